@@ -371,9 +371,6 @@ extern "C" int sph_bind(sph_ctx *c, void *workspace, size_t bytes, void *stream)
     r = hip_check(c, hipMemsetAsync(c->w.learn_step, 0, 4 * sizeof(int64_t), c->stream),
                   "clear learned-try counters");
     if (r) return r;
-    r = hip_check(c, hipMemsetAsync(c->w.wl_count, 0, sizeof(int64_t), c->stream),
-                  "clear worklist length");
-    if (r) return r;
     r = hip_check(c, hipMemsetAsync(c->w.dt_cur, 0, sizeof(double), c->stream), "clear dt");
     if (r) return r;
     r = hip_check(c, hipMemsetAsync(c->w.dt_prev, 0, sizeof(double), c->stream), "clear dt_prev");

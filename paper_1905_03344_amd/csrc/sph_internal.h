@@ -77,7 +77,7 @@ struct Workspace {
     uint8_t *refill;       // n_max
     int32_t *work;         // n_max: particles that need another count
     int32_t *wl;           // n_max: their worklist
-    int64_t *wl_count;     // 1: its length, zero between solves
+    int64_t *wl_count;     // 1: its length
     int64_t *learn_step;   // 4: accepted and missed tries of the current learned h solve, and
                            // whether the next one's tries count their shells (1) or not (0)
     double *hs_next, *hs_lo, *hs_hi, *hs_best_h, *hs_last_h;  // h iteration state, n_max each
