@@ -1,0 +1,77 @@
+"""The full-shell rule of learned tries (a try in the band is a miss where more
+than 48 particles lie in |r - 2h| < 2h/24) against counts of scipy's tree."""
+import numpy as np
+import pytest
+
+from paper_1905_03344_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def zero_model():
+    """Weights that predict no change: tries are at h_prev."""
+    w = inputs.mlp_init(3)
+    w["W3"] = 0.0 * w["W3"]
+    w["b3"] = 0.0 * w["b3"]
+    return w, np.array([0.0] * 6 + [1.0] * 6)
+
+
+def sheet(tiles=32):
+    """A sheet in a periodic unit box, tiles x tiles squares of 17 particles,
+    16 in the lower half and one in the upper: half a tile is a Morton cell, so
+    that one particle in 17 has no others in its group.  (In a plane a sixth
+    of the neighbours are in the shell.)"""
+    rng = np.random.default_rng(17)
+    n = 17 * tiles * tiles
+    ic = inputs.clumpy(n_clumps=1, per_clump=n - 8, n_background=8, seed=1)
+    tx, ty = np.divmod(np.arange(n) // 17, tiles)
+    up = np.arange(n) % 17 == 16
+    f = 0.02 + 0.96 * rng.random((2, n))
+    ic.x[:] = (tx + f[0]) / tiles
+    ic.y[:] = (ty + 0.5 * (up + f[1])) / tiles
+    ic.z[:] = 0.25 + 1e-5 * rng.random(n)
+    for a in (ic.vx, ic.vy, ic.vz):
+        a[:] = 0.0
+    ic.periodic, ic.box_lo, ic.box_hi = (1, 1, 1), (0.0,) * 3, (1.0,) * 3
+    return ic
+
+
+@pytest.mark.parametrize("n_target", [100, 260])
+def test_counts_beyond_the_held_hits(n_target):
+    """260 neighbours: more particles within the shell's outer radius than a
+    wave holds, about half of the shells full."""
+    from scipy.spatial import cKDTree
+    from paper_1905_03344_amd import ffi
+    from paper_1905_03344_amd.state import Simulation
+    ic = sheet()
+    ic.h[:] = 0.5 * np.sqrt(n_target / (np.pi * ic.n))
+    out = {}
+    for mode in (ffi.SPH_TRY_SHELL_NEVER, ffi.SPH_TRY_SHELL_ALWAYS):
+        print(f"shells n_target {n_target} mode {mode}", flush=True)
+        p = ffi.default_params()
+        p.n_target = n_target
+        sim = Simulation(ic, params=p, h_mode=ffi.SPH_H_LEARNED, learned_try_shell=mode,
+                         list_stride=512, extra_per_particle=512, walk_defer_group=1)
+        sim.set_mlp(*zero_model())
+        sim.evaluate()
+        h = sim.numpy("h")[np.argsort(sim.numpy("id"))]
+        sim.step(1e-12)
+        sim.sync()
+        o = np.argsort(sim.numpy("id"))
+        out[mode] = {f: sim.numpy(f)[o] for f in ("x", "y", "z", "flags")}
+        out[mode]["h_prev"] = h
+    a, b = out[ffi.SPH_TRY_SHELL_NEVER], out[ffi.SPH_TRY_SHELL_ALWAYS]
+    np.testing.assert_array_equal(a["h_prev"], b["h_prev"])
+    X = np.stack([a["x"], a["y"], a["z"]], axis=1)
+    tree = cKDTree(X, boxsize=1.0)
+    ball = lambda f: tree.query_ball_point(X, 2.0 * a["h_prev"] * f, return_length=True)
+    outer = ball(1.0 + 1.0 / 24.0)
+    full = outer - ball(1.0 - 1.0 / 24.0) > 48
+    took_a, took_b = (a["flags"] & 2) != 0, (b["flags"] & 2) != 0
+    assert took_a.mean() > 0.9
+    if n_target == 260:
+        # (the input has both kinds)
+        assert np.mean(outer > 257) > 0.9 and 0.05 < np.mean(full) < 0.95
+    # exactly the tries with a full shell are misses (no particle shares its
+    # neighbourhood with at most one other of its 64 in index order)
+    np.testing.assert_array_equal(took_b, took_a & ~full)
