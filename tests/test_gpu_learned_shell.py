@@ -36,22 +36,50 @@ def sheet(tiles=32):
     return ic
 
 
+def exempt(x, h, key, defer):
+    """Particles whose share of their 64 in index order is at most `defer`: the
+    64 are split by radius (within 3 of the smallest), then by Morton prefix
+    while they spread over more than 3 of the largest."""
+    out = np.zeros(len(h), dtype=bool)
+    for b in range(0, len(h), 64):
+        pending = np.arange(b, min(b + 64, len(h)))
+        while len(pending):
+            g = pending
+            while True:
+                r = 2.0 * h[g]
+                if r.max() > 3.0 * r.min():
+                    g = g[r <= 3.0 * r.min()]
+                    continue
+                if np.ptp(x[g], axis=0).max() <= 3.0 * r.max() or len(g) <= 2:
+                    break
+                top = int(key[g].min()) ^ int(key[g].max())
+                if top == 0:
+                    break
+                g = g[(key[g] ^ key[g[0]]) >> (top.bit_length() - 1) == 0]
+            out[g] = len(g) <= defer
+            pending = np.setdiff1d(pending, g)
+    return out
+
+
+@pytest.mark.parametrize("tiles", [32, 82])   # groups of up to 16 and of up to 64
+@pytest.mark.parametrize("prefilter", [0, 1])
 @pytest.mark.parametrize("n_target", [100, 260])
-def test_counts_beyond_the_held_hits(n_target):
+def test_counts_beyond_the_held_hits(n_target, prefilter, tiles):
     """260 neighbours: more particles within the shell's outer radius than a
     wave holds, about half of the shells full."""
     from scipy.spatial import cKDTree
     from paper_1905_03344_amd import ffi
     from paper_1905_03344_amd.state import Simulation
-    ic = sheet()
+    ic = sheet(tiles)
     ic.h[:] = 0.5 * np.sqrt(n_target / (np.pi * ic.n))
     out = {}
     for mode in (ffi.SPH_TRY_SHELL_NEVER, ffi.SPH_TRY_SHELL_ALWAYS):
-        print(f"shells n_target {n_target} mode {mode}", flush=True)
+        print(f"shells n {ic.n} n_target {n_target} prefilter {prefilter} mode {mode}", flush=True)
         p = ffi.default_params()
         p.n_target = n_target
         sim = Simulation(ic, params=p, h_mode=ffi.SPH_H_LEARNED, learned_try_shell=mode,
-                         list_stride=512, extra_per_particle=512, walk_defer_group=1)
+                         list_stride=512, extra_per_particle=512, walk_defer_group=1,
+                         walk_prefilter=prefilter)
         sim.set_mlp(*zero_model())
         sim.evaluate()
         h = sim.numpy("h")[np.argsort(sim.numpy("id"))]
@@ -60,6 +88,8 @@ def test_counts_beyond_the_held_hits(n_target):
         o = np.argsort(sim.numpy("id"))
         out[mode] = {f: sim.numpy(f)[o] for f in ("x", "y", "z", "flags")}
         out[mode]["h_prev"] = h
+        x = np.stack([sim.numpy(f) for f in ("x", "y", "z")], axis=1)
+        out[mode]["exempt"] = exempt(x, h[sim.numpy("id")], sim.numpy("key"), 1)[o]
     a, b = out[ffi.SPH_TRY_SHELL_NEVER], out[ffi.SPH_TRY_SHELL_ALWAYS]
     np.testing.assert_array_equal(a["h_prev"], b["h_prev"])
     X = np.stack([a["x"], a["y"], a["z"]], axis=1)
@@ -72,6 +102,6 @@ def test_counts_beyond_the_held_hits(n_target):
     if n_target == 260:
         # (the input has both kinds)
         assert np.mean(outer > 257) > 0.9 and 0.05 < np.mean(full) < 0.95
-    # exactly the tries with a full shell are misses (no particle shares its
-    # neighbourhood with at most one other of its 64 in index order)
-    np.testing.assert_array_equal(took_b, took_a & ~full)
+    assert np.mean(b["exempt"]) < 0.01
+    # exactly the tries with a full shell are misses
+    np.testing.assert_array_equal(took_b, took_a & (~full | b["exempt"]))
