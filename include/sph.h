@@ -96,7 +96,13 @@ typedef struct sph_ctx sph_ctx;
  * order are exempt).  AUTO: as ALWAYS for runs of 131,072 particles or more
  * (below 4,000,000, or with SPH_WALK_SHELL_FIRST; not with SPH_WALK_WORKLIST) while
  * more than a tenth of the previous learned solve's tries missed (not on the
- * first); else the rows as ALWAYS, no shells. */
+ * first after sph_bind, sph_evaluate or sph_mlp_set_weights); else the rows as
+ * ALWAYS, no shells.  So under AUTO a step depends on the one before it beyond
+ * the particles' state: a state put back into such a run continues alike only
+ * after sph_evaluate, or with NEVER or ALWAYS.
+ * The limit of 48 is made for n_target = 100, where an even distribution has 25
+ * in the shell; from an n_target of about 190 on nearly every try is a miss under
+ * ALWAYS, and under AUTO from the first solve with a tenth of misses on. */
 #define SPH_TRY_SHELL_AUTO 0
 #define SPH_TRY_SHELL_NEVER 1
 #define SPH_TRY_SHELL_ALWAYS 2
@@ -170,9 +176,11 @@ typedef struct sph_params {
                                * most this many (0 = default 4; 1..64) are counted one per
                                * wave afterwards; larger suits strongly clustered inputs.
                                * Speed only: sets, rows, h, counts and fields do not
-                               * depend on it. */
+                               * depend on it, but for the exemption of learned tries
+                               * from the full-shell rule (SPH_TRY_SHELL_ALWAYS, _AUTO). */
     int32_t volumes;        /* SPH_VOLUMES_STANDARD (default) or SPH_VOLUMES_GENERALIZED */
-    int32_t walk_strategy;  /* SPH_WALK_AUTO (default), _SHELL_FIRST or _WORKLIST (all the same)*/
+    int32_t walk_strategy;  /* SPH_WALK_AUTO (default), _SHELL_FIRST or _WORKLIST: of no
+                             * effect but in SPH_TRY_SHELL_AUTO's rule */
     double gve_exponent;    /* p of the generalized weights X = (m/rho)^p, in [0, 1] (0.7) */
     int32_t learned_try_shell; /* SPH_TRY_SHELL_AUTO (default), _NEVER or _ALWAYS */
     int32_t pad1;

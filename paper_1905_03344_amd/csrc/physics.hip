@@ -869,14 +869,18 @@ hipError_t launch_kick_drift(sph_ctx *c, sph_particles *s, double dt, const doub
 }
 
 // pv = v, pu = u: evaluation at the stored state (a step's predicted values
-// come with the permutation)
+// come with the permutation).  A run starts there: what learned solves left about
+// their misses (Workspace.learn_step) goes.
 __global__ __launch_bounds__(SPH_BLOCK) void k_copy_pred(
     int64_t n, const double *__restrict__ vx, const double *__restrict__ vy,
     const double *__restrict__ vz, const double *__restrict__ u, double *__restrict__ pvx,
-    double *__restrict__ pvy, double *__restrict__ pvz, double *__restrict__ pu)
+    double *__restrict__ pvy, double *__restrict__ pvz, double *__restrict__ pu,
+    int64_t *__restrict__ learn_step)
 {
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
+    if (i == 0)
+        for (int k = 0; k < 4; ++k) learn_step[k] = 0;
     pvx[i] = vx[i]; pvy[i] = vy[i]; pvz[i] = vz[i]; pu[i] = u[i];
 }
 
@@ -887,7 +891,7 @@ hipError_t launch_copy_pred(sph_ctx *c, sph_particles *s)
     int k = s->cur;
     hipLaunchKernelGGL(k_copy_pred, dim3((unsigned)ceil_div(n, SPH_BLOCK)), dim3(SPH_BLOCK), 0,
                        c->stream, n, s->vx[k], s->vy[k], s->vz[k], s->u[k], s->pvx, s->pvy, s->pvz,
-                       s->pu);
+                       s->pu, c->w.learn_step);
     return hipGetLastError();
 }
 

@@ -105,3 +105,91 @@ def test_counts_beyond_the_held_hits(n_target, prefilter, tiles):
     assert np.mean(b["exempt"]) < 0.01
     # exactly the tries with a full shell are misses
     np.testing.assert_array_equal(took_b, took_a & (~full | b["exempt"]))
+
+
+def _cloud(n):
+    """A power-law cloud: in many bands more than 48 particles in the shell."""
+    rng = np.random.default_rng(31)
+    ic = inputs.clumpy(n_clumps=1, per_clump=n - 8, n_background=8, seed=2)
+    r = rng.random(n) ** 2.5
+    u = rng.normal(size=(n, 3))
+    u *= (r / np.linalg.norm(u, axis=1))[:, None]
+    ic.x[:], ic.y[:], ic.z[:] = u[:, 0], u[:, 1], u[:, 2]
+    for a in (ic.vx, ic.vy, ic.vz):
+        a[:] = 0.0
+    ic.h[:] = np.maximum(0.5 * (100.0 / n) ** 0.4 * np.maximum(r, 1e-3) ** 0.87, 1e-5)
+    return ic
+
+
+def test_auto_follows_the_solve_before():
+    """AUTO at 140,003 particles: a first step, whose tries (2% above h_prev) miss
+    by more than a tenth, as NEVER, and a second one (tries at h_prev) as ALWAYS
+    from the same state; sph_evaluate and new weights start afresh."""
+    from paper_1905_03344_amd import ffi
+    from paper_1905_03344_amd.state import Simulation
+    NEVER, ALWAYS, AUTO = (ffi.SPH_TRY_SHELL_NEVER, ffi.SPH_TRY_SHELL_ALWAYS,
+                           ffi.SPH_TRY_SHELL_AUTO)
+    ic = _cloud(140003)
+    # y = 0.02 where the feature dt c / h is large, 0 where it is small
+    w, norm = zero_model()
+    for k in ("W1", "W2", "W3"):
+        w[k] = 0.0 * w[k]
+    w["W1"][0, 5], w["W2"][0, 0], w["W3"].reshape(-1)[0] = 1.0, 4.0, 0.02
+    norm[11] = 1e-10
+    far, near = 1e-8, 1e-18
+
+    def make(mode, like=None):
+        sim = Simulation(ic, h_mode=ffi.SPH_H_LEARNED, learned_try_shell=mode, list_stride=256,
+                         extra_per_particle=1024)
+        sim.set_mlp(w, norm)
+        if like is not None:
+            for f in ffi.CARRIED_F64 + ffi.CARRIED_I32:
+                sim.field(f).copy_(like.field(f))
+            sim.d_dt.copy_(like.d_dt)
+        return sim
+
+    def state(sim):
+        sim.sync()
+        return {f: sim.numpy(f).copy() for f in ("id", "h", "nc", "flags", "rho", "ax", "du")}
+
+    def same(a, b):
+        return all(np.array_equal(a[f], b[f]) for f in a)
+
+    sims = {m: make(m) for m in (NEVER, ALWAYS, AUTO)}
+    first = {}
+    for m, sim in sims.items():
+        print(f"first step, mode {m}", flush=True)
+        sim.evaluate()
+        sim.step(far)
+        first[m] = state(sim)
+    miss = 1.0 - np.mean((first[AUTO]["flags"] & 2) != 0)
+    assert 0.1 < miss < 0.9
+    assert same(first[AUTO], first[NEVER]) and not same(first[AUTO], first[ALWAYS])
+    auto = sims[AUTO]
+    twins = {m: make(m, like=auto) for m in (NEVER, ALWAYS)}
+    fresh, weights = make(AUTO, like=auto), make(AUTO, like=auto)
+    keep = {f: auto.field(f).clone() for f in ffi.CARRIED_F64 + ffi.CARRIED_I32}
+    keep_dt = auto.d_dt.clone()
+    print("second step", flush=True)
+    auto.step(near)
+    second = state(auto)
+    for m, sim in twins.items():
+        sim.step(near)
+        assert same(second, state(sim)) == (m == ALWAYS)
+    # the state put back: sph_evaluate, or new weights, and the next solve is
+    # a first one
+    for restart in ("evaluate", "weights"):
+        auto.step(far)
+        auto.sync()
+        for f, v in keep.items():
+            auto.field(f).copy_(v)
+        auto.d_dt.copy_(keep_dt)
+        other = fresh if restart == "evaluate" else weights
+        if restart == "evaluate":
+            auto.evaluate()
+            other.evaluate()
+        else:
+            auto.set_mlp(w, norm)
+        auto.step(near)
+        other.step(near)
+        assert same(state(auto), state(other)), restart
