@@ -387,10 +387,12 @@ int sph_copy_internal(sph_ctx *ctx, int which, void *dst, size_t bytes, size_t *
  * stage of every subsequent call (overhead: two event records per stage).
  * Stages: SPH_STAGE_CELLS (A1-A4), _HSOLVE (A5 and the gather sets),
  * _EXTRA (complement E), _DENSITY (A7), _EOS (A8), _FORCES (A9 + dt),
- * _INTEGRATE (A10 kicks, drift, prediction), _MLP (learned h prediction),
- * _HWALK (the counts of the h iteration, also counted in _HSOLVE: all of them
- * in the plain form; in the learned form the tries alone, the fallbacks being
- * the rest of _HSOLVE). */
+ * _INTEGRATE (A10 kicks and drift; the prediction rides with the permutation,
+ * in _CELLS), _MLP (learned h prediction), and inside _HSOLVE, counted there too:
+ * _HWALK (the counts of the h iteration, all of them in the plain form; in the
+ * learned form the tries alone, the fallbacks being the rest of _HSOLVE: the two
+ * forms' _HWALK are not alike) and _HFIRST (the first count of every particle
+ * alone, in both forms). */
 #define SPH_STAGE_CELLS 0
 #define SPH_STAGE_HSOLVE 1
 #define SPH_STAGE_EXTRA 2
@@ -400,7 +402,8 @@ int sph_copy_internal(sph_ctx *ctx, int which, void *dst, size_t bytes, size_t *
 #define SPH_STAGE_INTEGRATE 6
 #define SPH_STAGE_MLP 7          /* learned mode: feature build + MLP inference */
 #define SPH_STAGE_HWALK 8        /* inside _HSOLVE: its counts, or the learned tries */
-#define SPH_NSTAGES 9
+#define SPH_STAGE_HFIRST 9       /* inside _HWALK: the first counts */
+#define SPH_NSTAGES 10
 
 /* enable = 1 clears the accumulators and starts recording; 0 stops. */
 int sph_timing(sph_ctx *ctx, int enable);

@@ -466,7 +466,10 @@ static int find_neighbors_impl(sph_ctx *c, sph_particles *s, sph_nlist *nl, cons
         StageScope scope(c, SPH_STAGE_HSOLVE);
         {
             StageScope walk(c, SPH_STAGE_HWALK);
-            TRY(launch_hsolve(c, s, nl, h_try, 0), "h iteration (first counts)");
+            {
+                StageScope first(c, SPH_STAGE_HFIRST);
+                TRY(launch_hsolve(c, s, nl, h_try, 0), "h iteration (first counts)");
+            }
             if (!h_try) TRY(launch_hsolve(c, s, nl, h_try, 1), "h iteration");
         }
         if (h_try) TRY(launch_hsolve(c, s, nl, h_try, 1), "h iteration (fallbacks)");

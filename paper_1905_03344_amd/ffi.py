@@ -138,7 +138,8 @@ SPH_MLP_NFEAT = 8
 MLP_LAYOUT = {"W1": (0, (64, 6)), "b1": (384, (64,)), "W2": (448, (64, 64)),
               "b2": (4544, (64,)), "W3": (4608, (1, 64)), "b3": (4672, (1,))}
 
-STAGES = ("cells", "hsolve", "extra", "density", "eos", "forces", "integrate", "mlp", "hwalk")
+STAGES = ("cells", "hsolve", "extra", "density", "eos", "forces", "integrate", "mlp", "hwalk",
+          "hfirst")
 
 # entry points of the learned / mixed forms, bound when present
 _OPTIONAL = {}
@@ -275,12 +276,13 @@ def sph_timing(ctx, enable: bool):
     check(lib().sph_timing(ctx, int(bool(enable))), ctx)
 
 
-def sph_timing_read(ctx):
-    """{stage: (total_ms, intervals)} since timing was enabled."""
+def sph_timing_read(ctx, first=False):
+    """{stage: (total_ms, intervals)} since timing was enabled; with `first` also
+    "hfirst", the first counts alone (a part of "hwalk")."""
     ms = (ctypes.c_double * len(STAGES))()
     cnt = (_I64 * len(STAGES))()
     check(lib().sph_timing_read(ctx, ms, cnt, len(STAGES)), ctx)
-    return {s: (ms[k], cnt[k]) for k, s in enumerate(STAGES)}
+    return {s: (ms[k], cnt[k]) for k, s in enumerate(STAGES) if first or s != "hfirst"}
 
 
 # learned smoothing length ---------------------------------------------------
