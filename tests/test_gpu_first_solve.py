@@ -40,3 +40,22 @@ def test_first_solve_matches_oracle(scale, periodic, list_stride):
     np.testing.assert_array_equal(_gather_rows_flat(sim), st.lidx)
     assert stats.nonconverged == st.nonconv
     assert stats.h_counts > 1.875 * ic.n   # (nearly all missed)
+
+
+@pytest.mark.parametrize("search_div", [1, 3, 4])
+def test_first_solve_search_div(search_div):
+    """Cells of other widths: the walks of one particle take none below half a
+    radius.  The same sets."""
+    from paper_1905_03344_amd.state import Simulation
+    ic = inputs.square_patch(24, 8)
+    ic.h[:] *= 0.8
+    print(f"search_div {search_div}", flush=True)
+    st = O.State(ic.copy())
+    st.keep_gather = True
+    st.evaluate(method=1)
+    sim = Simulation(ic, extra_per_particle=128, search_div=search_div)
+    sim.evaluate()
+    sim.sync()
+    compare_cells(sim, st)
+    compare_neighbors(sim, st)
+    np.testing.assert_array_equal(_gather_rows_flat(sim), st.lidx)
