@@ -728,9 +728,6 @@ extern "C" int sph_mlp_set_weights(sph_ctx *c, const float *params, const double
                            c->stream), "upload standardisation");
     TRY(hipMemsetAsync(c->w.mlp_m, 0, SPH_MLP_ROW * sizeof(float), c->stream), "clear Adam");
     TRY(hipMemsetAsync(c->w.mlp_v, 0, SPH_MLP_ROW * sizeof(float), c->stream), "clear Adam");
-    // (the misses of other weights say nothing about these)
-    TRY(hipMemsetAsync(c->w.learn_step, 0, 4 * sizeof(int64_t), c->stream),
-        "clear learned-try counters");
     TRY(launch_mlp_refresh(c), "bf16 copy");
     TRY(hipStreamSynchronize(c->stream), "sync");   // host sources
     c->mlp_ready = 1;

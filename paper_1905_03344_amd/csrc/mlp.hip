@@ -688,11 +688,14 @@ __global__ __launch_bounds__(SPH_BLOCK) void k_norm_final(const double *__restri
     }
 }
 
-// bf16 copies of the master parameters
+// bf16 copies of new master parameters; what solves with others left about their
+// misses (Workspace.learn_step) says nothing about these
 __global__ __launch_bounds__(SPH_BLOCK) void k_mlp_refresh(const float *__restrict__ master,
-                                                           uint16_t *__restrict__ wb)
+                                                           uint16_t *__restrict__ wb,
+                                                           int64_t *__restrict__ learn_step)
 {
     int k = blockIdx.x * blockDim.x + threadIdx.x;
+    if (k < 4) learn_step[k] = 0;
     if (k < MLP_NP) wb[k] = bf16_bits_f(master[k]);
 }
 
@@ -814,7 +817,7 @@ hipError_t launch_mlp_adam(sph_ctx *c, const float *grad, double lr, double b1, 
 hipError_t launch_mlp_refresh(sph_ctx *c)
 {
     hipLaunchKernelGGL(k_mlp_refresh, dim3((unsigned)ceil_div(MLP_NP, SPH_BLOCK)), dim3(SPH_BLOCK),
-                       0, c->stream, c->w.mlp_master, c->w.mlp_wb);
+                       0, c->stream, c->w.mlp_master, c->w.mlp_wb, c->w.learn_step);
     return hipGetLastError();
 }
 
