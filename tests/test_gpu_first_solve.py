@@ -26,7 +26,7 @@ def _uniform(n, periodic):
 @pytest.mark.parametrize("scale,periodic", [(0.93, (0, 0, 0)), (0.88, (1, 0, 1))])
 def test_first_solve_matches_oracle(scale, periodic, list_stride):
     from paper_1905_03344_amd.state import Simulation
-    ic = _uniform(100003, periodic)
+    ic = _uniform(200003, periodic)
     ic.h[:] *= scale
     print(f"first solve n {ic.n} scale {scale} rows of {list_stride}", flush=True)
     st = O.State(ic.copy())
