@@ -525,13 +525,6 @@ __device__ __forceinline__ void block_add_i64(int64_t v, int64_t *addr)
     __syncthreads();  // the shared slots are reused by the next call
 }
 
-// orders this wave's global writes before its lanes' later reads of them
-__device__ __forceinline__ void wave_mem_sync()
-{
-    __threadfence_block();
-    __builtin_amdgcn_wave_barrier();
-}
-
 // K block totals, each added to a counter (and to a second one where given)
 // by one atomic; one barrier for all
 template <int K>

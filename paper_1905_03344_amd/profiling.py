@@ -2,11 +2,11 @@
 
     python -m paper_1905_03344_amd.profiling traffic \\
         --fetch F.csv --write W.csv --copy-fetch CF.csv --copy-write CW.csv \\
-        --kernel "void k_hsolve_round<64, false>" --source neighbors.hip \\
+        --kernel "void k_hsolve_round<64, false, true>" --source neighbors.hip \\
         --workload square_patch_100^3_1M_fp64 --last 2 --out profiles/X_traffic.json
     python -m paper_1905_03344_amd.profiling stats --csv run_kernel_stats.csv --top 12
     python -m paper_1905_03344_amd.profiling counters --csv A.csv B.csv \\
-        --kernel "void k_hsolve_round<64, false>" --source neighbors.hip \\
+        --kernel "void k_hsolve_round<64, false, true>" --source neighbors.hip \\
         --workload "square_patch_400^3_64M" [--traffic T.json --duration-us D] --out C.json
 
 `traffic` turns two counter runs (FETCH_SIZE, then WRITE_SIZE, KiB per
